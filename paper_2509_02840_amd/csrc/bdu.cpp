@@ -67,11 +67,6 @@ Plan *get_plan(int64_t m, int64_t n, int k0, int nw, bool upload, hipError_t *er
         size_t cb = sizeof(GenChain) * p->chains.size();
         hipError_t e = hipMalloc(&p->d_chains, cb);
         if (e == hipSuccess) e = hipMemcpy(p->d_chains, p->chains.data(), cb, hipMemcpyHostToDevice);
-        if (e == hipSuccess && !p->starts.empty()) {
-            size_t sb = sizeof(GenStart) * p->starts.size();
-            e = hipMalloc(&p->d_starts, sb);
-            if (e == hipSuccess) e = hipMemcpy(p->d_starts, p->starts.data(), sb, hipMemcpyHostToDevice);
-        }
         for (int s = 0; s < 2 && e == hipSuccess; ++s) {
             size_t bb = sizeof(BlockDesc) * p->blocks[s].size();
             e = hipMalloc(&p->d_blocks[s], bb);
@@ -303,14 +298,14 @@ int ensure_rcap(bdu_ctx *h, int r)
 
 // Rotation stages of one pass (spike, generation, application) for `count`
 // handles listed in the device array hs (all with the same tiling).
-hipError_t run_rotation_stages(HandleDev *const *hs, int count, bool any_spike, int64_t lds_bytes,
+hipError_t run_rotation_stages(HandleDev *const *hs, int count, bool any_spike, int64_t rows,
                                bool in_lds, int gen_threads, int max_panels, int k0, int nw, int rpl, Gate gate,
                                hipStream_t st)
 {
     hipError_t e = hipSuccess;
     if (any_spike) e = timed(ST_SPIKE, st, [&] { return launch_spike(hs, count, gate, st); });
     if (e == hipSuccess)
-        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, lds_bytes, in_lds, gen_threads, gate, st); });
+        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, rows, in_lds, gen_threads, gate, st); });
     if (e == hipSuccess)
         e = timed(ST_APPLY, st, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, gate, st); });
     return e;
@@ -321,7 +316,7 @@ hipError_t run_rotation_stages(HandleDev *const *hs, int count, bool any_spike, 
 // generated on st, and st waits for the application.
 //   st: [spike] gen 1 -> e1 -> gen 2 -> e2 ............ wait e3
 //   sd:          wait e1 -> apply 1 -> wait e2 -> apply 2 -> e3
-hipError_t run_split_stages(HandleDev *const *hs, int count, bool any_spike, int64_t lds_bytes, bool in_lds,
+hipError_t run_split_stages(HandleDev *const *hs, int count, bool any_spike, int64_t rows, bool in_lds,
                             int gen_threads, int max_panels, int k0, int nw, int rpl, Gate gate, hipStream_t st,
                             hipStream_t sd, hipEvent_t e1, hipEvent_t e2, hipEvent_t e3)
 {
@@ -331,10 +326,10 @@ hipError_t run_split_stages(HandleDev *const *hs, int count, bool any_spike, int
     hipError_t e = hipSuccess;
     if (any_spike) e = timed(ST_SPIKE, st, [&] { return launch_spike(hs, count, g1, st); });
     if (e == hipSuccess)
-        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, lds_bytes, in_lds, gen_threads, g1, st); });
+        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, rows, in_lds, gen_threads, g1, st); });
     if (e == hipSuccess) e = hipEventRecord(e1, st);
     if (e == hipSuccess)
-        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, lds_bytes, in_lds, gen_threads, g2, st); });
+        e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, rows, in_lds, gen_threads, g2, st); });
     if (e == hipSuccess) e = hipEventRecord(e2, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd, e1, 0);
     if (e == hipSuccess)
@@ -356,7 +351,7 @@ hipError_t run_split_stages(HandleDev *const *hs, int count, bool any_spike, int
 // spike's survivor), waits for it; the generator reloads u_N at the start
 // of every later segment.  Segment 0's application, which applies the
 // spike's rotations, follows it on sd.
-hipError_t run_segment_stages(HandleDev *const *hs, int count, bool any_spike, int64_t lds_bytes, bool in_lds,
+hipError_t run_segment_stages(HandleDev *const *hs, int count, bool any_spike, int64_t rows, bool in_lds,
                               int gen_threads, int max_panels, int k0, int nw, int rpl, Gate gate, int nseg,
                               hipStream_t st, hipStream_t sd, const hipEvent_t *ev, hipEvent_t done,
                               int fold_seg = 0, hipEvent_t spk_in = nullptr, hipEvent_t spk_out = nullptr)
@@ -378,7 +373,7 @@ hipError_t run_segment_stages(HandleDev *const *hs, int count, bool any_spike, i
         gk.part = 3 + k;
         if (beside && k == fold_seg) e = hipStreamWaitEvent(st, spk_out, 0);
         if (e == hipSuccess)
-            e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, lds_bytes, in_lds, gen_threads, gk, st); });
+            e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, rows, in_lds, gen_threads, gk, st); });
         if (e == hipSuccess) e = hipEventRecord(ev[k], st);
     }
     for (int k = 0; k < nseg && e == hipSuccess; ++k) {
@@ -407,19 +402,19 @@ int pass_single(bdu_ctx *h, int pass, bool project, const double *xb = nullptr, 
     if (project)
         e = timed(ST_PROJECT, st,
                   [&] { return launch_project(h->d_self, 1, tiles_of(h), Gate{nullptr, pass, 0, xb, xc}, st); });
-    const int64_t lds = gen_lds_bytes(h->n, h->plan->N);
+    const int64_t rows = h->plan->N;
     const int L = h->plan->L, np = panels_of(h), k0 = h->plan->K0, nw = h->plan->NW;
     if (e == hipSuccess && h->side && h->plan->nseg > 0 && h->seg[0]) {
         // sp1 and sp2 (the split pass's events) order the spike beside the
         // generation
-        e = run_segment_stages(h->d_self, 1, h->m > h->n, lds, h->lds_gen, L, np, k0, nw, h->rpl,
+        e = run_segment_stages(h->d_self, 1, h->m > h->n, rows, h->lds_gen, L, np, k0, nw, h->rpl,
                                Gate{nullptr, pass, 0}, h->plan->nseg, st, h->side, h->seg, h->sp3,
                                h->plan->fold_seg, h->sp1, h->sp2);
     } else if (e == hipSuccess && h->side) {
-        e = run_split_stages(h->d_self, 1, h->m > h->n, lds, h->lds_gen, L, np, k0, nw, h->rpl, Gate{nullptr, pass, 0},
+        e = run_split_stages(h->d_self, 1, h->m > h->n, rows, h->lds_gen, L, np, k0, nw, h->rpl, Gate{nullptr, pass, 0},
                              st, h->side, h->sp1, h->sp2, h->sp3);
     } else if (e == hipSuccess) {
-        e = run_rotation_stages(h->d_self, 1, h->m > h->n, lds, h->lds_gen, L, np, k0, nw, h->rpl,
+        e = run_rotation_stages(h->d_self, 1, h->m > h->n, rows, h->lds_gen, L, np, k0, nw, h->rpl,
                                 Gate{nullptr, pass}, st);
     }
     if (e != hipSuccess) {
@@ -470,10 +465,10 @@ void release_streams(bdu_ctx *h)
     h->side = nullptr;
 }
 
-bool gen_lds_fits(int64_t n, int64_t N)
+bool gen_lds_fits(int64_t N)
 {
     std::lock_guard<std::mutex> lk(g_mu);
-    return g_gen_lds && gen_lds_bytes(n, N) <= kMaxGenLds;
+    return g_gen_lds && N <= kMaxGenLdsRows;
 }
 
 // Applier tiling for a new handle of shape (m, n).
@@ -513,7 +508,7 @@ struct bdu_batch_ctx {
     struct Group {
         int k0, nw, rpl;
         bool spike, in_lds;
-        int64_t lds;
+        int64_t rows;  // largest N of the group
         int tiles, panels, off, cnt;
         int gen_threads;  // largest plan thread count of the group
         bool split;       // every member's pass splits after phase 1
@@ -600,7 +595,7 @@ int batch_build(const bdu_handle *hs, int count, int maxr, bool graph, bdu_batch
         auto &x = b->groups[g];
         members[g].push_back(i);
         x.spike |= h->m > h->n;
-        x.lds = std::max<int64_t>(x.lds, gen_lds_bytes(h->n, h->plan->N));
+        x.rows = std::max(x.rows, h->plan->N);
         x.gen_threads = std::max(x.gen_threads, h->plan->L);
         x.tiles = std::max(x.tiles, tiles_of(h));
         x.panels = std::max(x.panels, panels_of(h));
@@ -660,13 +655,13 @@ hipError_t batch_launch(bdu_batch b)
             const Gate gate{b->d_ranks + g.off, p};
             hipError_t e = timed(ST_PROJECT, st, [&] { return launch_project(arr, g.cnt, g.tiles, gate, st); });
             if (e == hipSuccess && g.nseg > 0 && b->side)
-                e = run_segment_stages(arr, g.cnt, g.spike, g.lds, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
+                e = run_segment_stages(arr, g.cnt, g.spike, g.rows, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
                                        g.rpl, gate, g.nseg, st, b->side, b->seg, b->sp3);
             else if (e == hipSuccess && g.split && b->side)
-                e = run_split_stages(arr, g.cnt, g.spike, g.lds, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
+                e = run_split_stages(arr, g.cnt, g.spike, g.rows, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
                                      g.rpl, gate, st, b->side, b->sp1, b->sp2, b->sp3);
             else if (e == hipSuccess)
-                e = run_rotation_stages(arr, g.cnt, g.spike, g.lds, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
+                e = run_rotation_stages(arr, g.cnt, g.spike, g.rows, g.in_lds, g.gen_threads, g.panels, g.k0, g.nw,
                                         g.rpl, gate, st);
             if (e != hipSuccess) return e;
         }
@@ -723,7 +718,7 @@ int64_t bdu_footprint_bytes(int64_t m, int64_t n)
     const int64_t ldq = (m + 127) / 128 * 128, ldp = (n + 127) / 128 * 128;
     int64_t bytes = 8 * (ldq * m + ldp * n + 2 * n + 2 * (m + n) + 2 * (m + n));
     bytes += 16 * (p->slots[0] + p->slots[1] + 2 * (4 * (int64_t)p->K + 64) + std::max<int64_t>(p->nspike, 1));
-    bytes += gen_lds_bytes(n, N);  // band (device memory or the image between split parts)
+    bytes += gen_band_bytes(n, N);  // band (device memory or the image between split parts)
     return bytes;
 }
 
@@ -786,7 +781,7 @@ int create_impl(int64_t m, int64_t n, const double *Q, const double *d, const do
     h->n = n;
     h->plan = plan;
     h->rpl = rpl;
-    h->lds_gen = gen_lds_fits(n, plan->N);
+    h->lds_gen = gen_lds_fits(plan->N);
     HandleDev &hd = h->hd;
     hipError_t a = hipSuccess;
     auto A = [&](hipError_t x) { if (a == hipSuccess) a = x; };
@@ -807,7 +802,7 @@ int create_impl(int64_t m, int64_t n, const double *Q, const double *d, const do
     A(dalloc(h.get(), &hd.csSp, plan->nspike));
     // the band in device memory (large n), or the image of the LDS band
     // kept between the two parts of a split generation
-    A(dalloc(h.get(), &hd.band, gen_lds_bytes(n, plan->N) / 8));
+    A(dalloc(h.get(), &hd.band, gen_band_bytes(n, plan->N) / 8));
     A(dalloc(h.get(), &hd.carry, 4 * kGenThreads));
     A(dalloc(h.get(), &h->d_hd, 1));
     A(dalloc(h.get(), &h->d_self, 1));
@@ -819,7 +814,6 @@ int create_impl(int64_t m, int64_t n, const double *Q, const double *d, const do
     }
     h->rcap = 1;
     hd.chains = plan->d_chains;
-    hd.starts = plan->d_starts;
     hd.blkL = plan->d_blocks[0];
     hd.blkR = plan->d_blocks[1];
     hd.ticks = plan->ticks;

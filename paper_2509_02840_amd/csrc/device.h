@@ -10,8 +10,6 @@ namespace bdu {
 
 constexpr int kMaxSeg = 8;  // most phase-2 segments of a split pass
 
-struct GenStart;
-
 // Everything a kernel needs to update one factorization A = Q Bd P^T.
 // Q is m x m and P is n x n, column-major; their leading dimensions ldq, ldp
 // are m and n rounded up to a multiple of 128 (the padding rows are zero).
@@ -23,7 +21,6 @@ struct HandleDev {
     double2 *csSp;          // spike rotations, in order
     double *band;           // global band scratch for large n (else unused)
     const GenChain *chains; // non-empty chains, schedule order
-    const GenStart *starts; // their first two rotations decoded (in-LDS generation; else null)
     const BlockDesc *blkL, *blkR;
     int64_t ticks;          // generation ticks
     int32_t m, n, N, nchains, nb1, nb2;
@@ -75,11 +72,19 @@ __host__ __device__ inline bool part_blocks(const H *h, int part, int *bbeg, int
 
 constexpr int kGenThreads = 1024;  // at n = 2048, 256 threads leave chains waiting for a free thread
 
-// Band storage of the generation kernel: row r (1-based, -3..N+4) starts at
+// The in-LDS generation kernel runs kGenStep ticks between barriers: chains
+// of one chunk of kGenChunk (one wavefront's) are ordered by tick, chains of
+// different chunks by step of kGenStep ticks.
+constexpr int kGenStep = 8, kGenChunk = 64;
+
+// Most rows N of a factorization whose generation fits in LDS (48 bytes a
+// row: four band cells, u and v).
+constexpr int64_t kMaxGenLds = 160 * 1024, kMaxGenLdsRows = 3392;
+
+// Band storage of the device-memory generation kernel: row r (1-based, -3..N+4) starts at
 // band_row(r) and holds the entries in columns r-2..r+3, column c at offset
 // c - r + 2.  The extra double every three rows spreads the rows that
-// neighbouring lanes touch in one tick (about seven rows apart) over the LDS
-// banks (with a plain stride of six they fall on a few banks), and keeps
+// neighbouring lanes touch in one tick over the cache lines' banks, and keeps
 // band_row(r + 3) = band_row(r) + 19, so a chain's addresses move by a
 // constant from one step of its pattern to the next.
 __host__ __device__ inline int band_row(int r)
@@ -95,15 +100,15 @@ __host__ __device__ inline int64_t band_doubles(int64_t N)
     return 6 * (N + 8) + (N + 8) / 3 + 2;
 }
 
-// LDS bytes the generation kernel needs for n columns and N rows.
-inline int64_t gen_lds_bytes(int64_t n, int64_t N)
+// Bytes of a handle's band in device memory for n columns and N rows: the
+// device-memory kernel's band, u and v, or the in-LDS kernel's image between
+// the parts of a pass (5 N + n + 18 doubles, fewer).
+inline int64_t gen_band_bytes(int64_t n, int64_t N)
 {
     return 8 * (band_doubles(N) + (N + 8) + (n + 8) + 2);
 }
 
-constexpr int64_t kMaxGenLds = 160 * 1024;
-
-// Rotation s of a chain as the generation kernel addresses it: the offsets
+// Rotation s of a chain as the device-memory generation kernel addresses it: the offsets
 // (in doubles from the band's start) of its five window pairs (x[k], y[k])
 // in the kernel's slot order and of its u or v pair, and its side.
 //
@@ -160,18 +165,5 @@ __host__ __device__ inline RotOff rot_offsets(int type, int param, int s, int uo
     }
     return o;
 }
-
-// A chain's first two rotations as the in-LDS generation kernel starts it,
-// decoded once per shape on the host: the offsets of rotation s_e (the one
-// at an even tick: 1 when the chain starts at an odd tick, else 0) in the
-// low 16 bits and of the other in the high 16 bits, in the order x[0..4],
-// y[0..4], vb; bit 0 of sides is the side of rotation s_e, bit 1 that of the
-// other.  Offsets fit in 16 bits whenever the band does in LDS; entries of
-// a rotation past the chain's end are 0 and never used.
-struct GenStart {
-    uint32_t off[11];
-    int32_t sides;
-};
-static_assert(sizeof(GenStart) == 48, "the generation kernel reads 12 words per chain");
 
 }  // namespace bdu

@@ -7,7 +7,9 @@
 //    rotation it performs comes strictly after every earlier rotation whose
 //    band rows overlap (so every band entry sees its updates in schedule
 //    order), and only once its thread has finished the previous chain.  The
-//    earliest such tau0 is taken chain by chain.
+//    earliest such tau0 is taken chain by chain when the band is in device
+//    memory (scan_ticks); the in-LDS kernel's are in closed form
+//    (chunk_ticks).
 // 3. Applier blocks for the left (Q) and right (P) rotation streams.
 #include "plan.h"
 
@@ -78,6 +80,111 @@ static void stage_starts(std::vector<BlockDesc> &blk, int64_t ncols, int K0, int
     }
 }
 
+// A chain starts at the earliest tick at which each of its rotations runs
+// after every earlier rotation (schedule order) that touches one of the
+// same entries: a band cell (rows x columns within offsets -2..3), u or v.
+// A left rotation on rows (i, i+1) touches columns i-1..i+3 of them and
+// u_i, u_{i+1}; a right rotation on columns (j, j+1) rows j-2..j+2 and
+// v_j, v_{j+1} (the only entries the schedule can make nonzero there).
+static void scan_ticks(Plan &P)
+{
+    std::vector<GenChain> &ch = P.chains;
+    const int N = (int)P.N, nn = (int)P.n;
+    const int off = 5;  // rows and columns -4 .. N+5
+    const int W = N + 12;
+    std::vector<int64_t> lastcell((size_t)W * 6, -1), lastu(W, -1), lastv(W, -1);
+    auto cells = [&](const Rot &r, auto &&fn) {
+        if (r.side == 0) {
+            for (int row = r.i; row <= r.i + 1; ++row)
+                for (int c = r.i - 1; c <= r.i + 3; ++c)
+                    if (c - row >= -2 && c - row <= 3) fn(lastcell[(size_t)(row + off) * 6 + (c - row + 2)]);
+            fn(lastu[r.i + off]);
+            fn(lastu[r.i + 1 + off]);
+        } else {
+            for (int row = r.i - 2; row <= r.i + 2; ++row)
+                for (int c = r.i; c <= r.i + 1; ++c)
+                    if (c - row >= -2 && c - row <= 3) fn(lastcell[(size_t)(row + off) * 6 + (c - row + 2)]);
+            fn(lastv[r.i + off]);
+            fn(lastv[r.i + 1 + off]);
+        }
+    };
+    auto fold_cells = [&](auto &&fn) {  // (N-1, n), (N, n), u_{N-1}, u_N, v_n
+        fn(lastcell[(size_t)(N - 1 + off) * 6 + (nn - (N - 1) + 2)]);
+        fn(lastcell[(size_t)(N + off) * 6 + (nn - N + 2)]);
+        fn(lastu[N - 1 + off]);
+        fn(lastu[N + off]);
+        fn(lastv[nn + off]);
+    };
+    const int L = P.L;
+    std::vector<int64_t> lane_free(L, 0);
+    int64_t tend = 0;
+    for (size_t c = 0; c < ch.size(); ++c) {
+        GenChain &g = ch[c];
+        int64_t tau0 = 0;
+        for (int s = 0; s < g.len; ++s) {
+            auto need = [&](int64_t &t) { tau0 = std::max(tau0, t + 1 - s); };
+            if (g.type == CH_FOLD) fold_cells(need);
+            else cells(decode(g.type, g.param, s), need);
+        }
+        int lane = (int)(c % L);
+        tau0 = std::max(tau0, lane_free[lane]);
+        for (int s = 0; s < g.len; ++s) {
+            auto mark = [&](int64_t &t) { t = std::max(t, tau0 + s); };
+            if (g.type == CH_FOLD) {
+                fold_cells(mark);
+            } else {
+                Rot r = decode(g.type, g.param, s);
+                cells(r, mark);
+                if (r.side == 0) ++P.nleft; else ++P.nright;
+            }
+        }
+        lane_free[lane] = tau0 + g.len;
+        g.tau0 = (int32_t)tau0;
+        tend = std::max(tend, tau0 + g.len);
+    }
+    P.ticks = tend;
+}
+
+// Ticks of the in-LDS generation kernel.  Chains of one phase start at
+// consecutive positions (gen.hip), one tick apart in phase 1 and three in
+// phase 2: the earliest starts at which every rotation follows the earlier
+// ones that touch one of its cells (checked rotation by rotation in
+// tests/test_host_schedule.py).  Each chunk of kGenChunk chains starts
+// kGenStep ticks late, so that two chains of different chunks meet a common
+// cell in different steps.  A chunk is held back by whole steps until each of
+// its threads has finished its previous chain by the step before.
+static void chunk_ticks(Plan &P)
+{
+    std::vector<GenChain> &ch = P.chains;
+    const int64_t L = P.L, nch1 = 2 * P.n - (P.m > P.n ? 2 : 3);
+    auto up = [](int64_t t) { return (t + kGenStep - 1) / kGenStep * kGenStep; };
+    auto place = [&](size_t first, size_t last, int64_t base, int64_t apart) {
+        std::vector<int64_t> end;  // by index in the phase
+        int64_t held = 0, tend = base;
+        for (size_t x = first; x < last; ++x) {
+            GenChain &g = ch[x];
+            // R(n) would start chain 2 n - 3 of phase 2: its index stays empty
+            const int64_t c = chain_in_phase(g.type, g.param);
+            const int64_t tau = base + apart * c + kGenStep * (c / kGenChunk);
+            end.resize((size_t)c, base);
+            if (c % kGenChunk == 0)
+                for (int64_t k = c; k < c + kGenChunk; ++k)
+                    if (k >= L && k - L < c)
+                        held = std::max(held, up(end[(size_t)(k - L)] - (tau + apart * (k - c))));
+            g.tau0 = (int32_t)(tau + held);
+            end.push_back(up(g.tau0 + g.len));
+            tend = std::max<int64_t>(tend, g.tau0 + g.len);
+            for (int s = 0; s < g.len && s < 2; ++s)
+                (decode(g.type, g.param, s).side == 0 ? P.nleft : P.nright) += (g.len - s + 1) / 2;
+        }
+        return tend;
+    };
+    const size_t fold = (size_t)nch1;
+    const int64_t end1 = place(0, fold, 0, 1);
+    ch[fold].tau0 = (int32_t)end1;
+    P.ticks = place(fold + 1, ch.size(), up(end1 + 1), 3);
+}
+
 // Segments of a single-handle pass (more segments hide more of the
 // application behind generation; each costs a generation launch with its
 // band save and reload and an applier launch).  Measured on one stream:
@@ -110,70 +217,13 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
     }
     P->nspike = (m > n) ? (m - n - 1) : 0;
 
-    // ---- generation ticks -------------------------------------------------
-    // A chain starts at the earliest tick at which each of its rotations runs
-    // after every earlier rotation (schedule order) that touches one of the
-    // same entries: a band cell (rows x columns within offsets -2..3), u or v.
-    // A left rotation on rows (i, i+1) touches columns i-1..i+3 of them and
-    // u_i, u_{i+1}; a right rotation on columns (j, j+1) rows j-2..j+2 and
-    // v_j, v_{j+1} (the only entries the schedule can make nonzero there).
-    const int off = 5;  // rows and columns -4 .. N+5
-    const int W = N + 12;
-    std::vector<int64_t> lastcell((size_t)W * 6, -1), lastu(W, -1), lastv(W, -1);
-    auto cells = [&](const Rot &r, auto &&fn) {
-        if (r.side == 0) {
-            for (int row = r.i; row <= r.i + 1; ++row)
-                for (int c = r.i - 1; c <= r.i + 3; ++c)
-                    if (c - row >= -2 && c - row <= 3) fn(lastcell[(size_t)(row + off) * 6 + (c - row + 2)]);
-            fn(lastu[r.i + off]);
-            fn(lastu[r.i + 1 + off]);
-        } else {
-            for (int row = r.i - 2; row <= r.i + 2; ++row)
-                for (int c = r.i; c <= r.i + 1; ++c)
-                    if (c - row >= -2 && c - row <= 3) fn(lastcell[(size_t)(row + off) * 6 + (c - row + 2)]);
-            fn(lastv[r.i + off]);
-            fn(lastv[r.i + 1 + off]);
-        }
-    };
-    auto fold_cells = [&](auto &&fn) {  // (N-1, n), (N, n), u_{N-1}, u_N, v_n
-        fn(lastcell[(size_t)(N - 1 + off) * 6 + (nn - (N - 1) + 2)]);
-        fn(lastcell[(size_t)(N + off) * 6 + (nn - N + 2)]);
-        fn(lastu[N - 1 + off]);
-        fn(lastu[N + off]);
-        fn(lastv[nn + off]);
-    };
     // With fewer chains than threads every chain gets its own thread, so
     // the workgroup only needs that many (rounded to whole wavefronts):
-    // fewer wavefronts meet at every tick's barrier.
-    const int L = (int)std::min<int64_t>(gen_threads, std::max<int64_t>(64, ((int64_t)ch.size() + 63) / 64 * 64));
-    P->L = L;
-    std::vector<int64_t> lane_free(L, 0);
-    int64_t tend = 0;
-    for (size_t c = 0; c < ch.size(); ++c) {
-        GenChain &g = ch[c];
-        int64_t tau0 = 0;
-        for (int s = 0; s < g.len; ++s) {
-            auto need = [&](int64_t &t) { tau0 = std::max(tau0, t + 1 - s); };
-            if (g.type == CH_FOLD) fold_cells(need);
-            else cells(decode(g.type, g.param, s), need);
-        }
-        int lane = (int)(c % L);
-        tau0 = std::max(tau0, lane_free[lane]);
-        for (int s = 0; s < g.len; ++s) {
-            auto mark = [&](int64_t &t) { t = std::max(t, tau0 + s); };
-            if (g.type == CH_FOLD) {
-                fold_cells(mark);
-            } else {
-                Rot r = decode(g.type, g.param, s);
-                cells(r, mark);
-                if (r.side == 0) ++P->nleft; else ++P->nright;
-            }
-        }
-        lane_free[lane] = tau0 + g.len;
-        g.tau0 = (int32_t)tau0;
-        tend = std::max(tend, tau0 + g.len);
-    }
-    P->ticks = tend;
+    // fewer wavefronts meet at every barrier.
+    P->L = (int)std::min<int64_t>(gen_threads, std::max<int64_t>(64, ((int64_t)ch.size() + 63) / 64 * 64));
+    if (P->N <= kMaxGenLdsRows) chunk_ticks(*P);
+    else scan_ticks(*P);
+    const int64_t tend = P->ticks;
     // Phase 1 (with the fold) ends at the tick its last chain finishes; the
     // pass can be generated in two parts split there when no chain is in
     // flight at that tick and no phase-2 chain starts before it (then the
@@ -238,31 +288,6 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
             g.slot[r.side] = bd.off + (int64_t)(lam0 / 3 + tl + w * S) * K + w * K0 + pos;
         }
     }
-    // the first two rotations of each chain, decoded for the in-LDS
-    // generation kernel (in the order of its even- and odd-tick sets)
-    {
-        const int uo = (int)band_doubles(N), vo = uo + (N + 8);
-        if ((int64_t)vo + nn + 8 <= 65536) {
-            P->starts.resize(ch.size());
-            for (size_t c = 0; c < ch.size(); ++c) {
-                const GenChain &g = ch[c];
-                GenStart &st = P->starts[c];
-                for (uint32_t &o : st.off) o = 0;
-                st.sides = 0;
-                if (g.type == CH_FOLD) continue;
-                const int se = (g.tau0 & 1) ? 1 : 0;
-                for (int set = 0; set < 2; ++set) {
-                    const int s = set == 0 ? se : 1 - se;
-                    if (s >= g.len) continue;
-                    const RotOff o = rot_offsets(g.type, g.param, s, uo, vo);
-                    const int v[11] = {o.x[0], o.x[1], o.x[2], o.x[3], o.x[4], o.y[0], o.y[1], o.y[2], o.y[3], o.y[4],
-                                       o.vb};
-                    for (int k = 0; k < 11; ++k) st.off[k] |= (uint32_t)v[k] << (16 * set);
-                    st.sides |= o.side << set;
-                }
-            }
-        }
-    }
     // ---- segments of a pass ---------------------------------------------
     // Applier block b (phase-1 blocks, then phase-2 blocks) holds the chains
     // of in-phase index [bK, bK + K) of its phase on both sides; blocks
@@ -281,11 +306,13 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
         }
         for (int b = 1; b < nbt; ++b) done[b] = std::max(done[b], done[b - 1]);
         const int want = std::min(nn >= 256 ? kSegments : kSegmentsSmall, nbt);
+        // the in-LDS kernel stops between steps
+        auto up = [](int64_t t) { return (t + kGenStep - 1) / kGenStep * kGenStep; };
         int64_t prev_t = 0;
         int prev_c = 0;
         for (int k = 1; k <= want; ++k) {
             const int c = k == want ? nbt : (int)((int64_t)nbt * k / want);
-            const int64_t t = k == want ? P->ticks : done[c - 1];
+            const int64_t t = k == want ? P->ticks : P->N <= kMaxGenLdsRows ? up(done[c - 1]) : done[c - 1];
             if (c <= prev_c || t <= prev_t || (k < want && t >= P->ticks)) continue;
             P->bcut[P->nseg] = c;
             P->tcut[P->nseg] = (int32_t)t;

@@ -55,26 +55,27 @@ __device__ __forceinline__ void givens_m(double a, double b, double &c, double &
     r = ident ? (m1 ? b : a) : rs * unsc;
 }
 
-// The same generator, faster when the magnitudes of a and b lie in
-// [2^-370, 2^370] on every active lane of the wavefront (a wave-uniform
-// test; otherwise the general form above runs).  In that range no scaling
-// applies, the target is nonzero, r^2 = a^2 + b^2 is at least 2^-740, and
-// both quotients and 1/r are normal numbers, so the IEEE square root and the
-// two IEEE divisions by r reduce to their core sequences with the same
-// correctly rounded results: the square root as an rsq estimate with two
-// Newton-Raphson corrections, each division as the reciprocal refined twice,
-// the product and one residual correction.  Their scaling and special-value
-// steps only change operands outside the range.  The two divisions share
-// the reciprocal of r.
-template <int MODE>
-__device__ __forceinline__ void givens_fast(double a, double b, double &c, double &s, double &r)
+// Whether the magnitudes of a and b lie in [2^-370, 2^370] (2^371 above, by
+// the exponents alone).
+__device__ __forceinline__ bool givens_in_range(double a, double b)
 {
-    const double fa = fabs(a), fb = fabs(b);
-    const bool in = fa >= 0x1p-370 && fa <= 0x1p370 && fb >= 0x1p-370 && fb <= 0x1p370;
-    if (!__all(in)) {
-        givens_m<MODE>(a, b, c, s, r);
-        return;
-    }
+    const uint32_t ea = __builtin_amdgcn_ubfe((uint32_t)__double2hiint(a), 20, 11);
+    const uint32_t eb = __builtin_amdgcn_ubfe((uint32_t)__double2hiint(b), 20, 11);
+    return ea - (1023u - 370u) <= 740u && eb - (1023u - 370u) <= 740u;
+}
+
+// The same generator for a and b in that range.  There no scaling applies,
+// the target is nonzero, r^2 = a^2 + b^2 is at least 2^-740, and both
+// quotients and 1/r are normal numbers, so the IEEE square root and the two
+// IEEE divisions by r reduce to their core sequences with the same correctly
+// rounded results: the square root as an rsq estimate refined once together
+// with half the reciprocal root h and two residual corrections; 1/r from 2 h
+// by one Newton-Raphson step, which leaves it within rounding of 1/r; each
+// quotient as the product and one residual correction.  The two divisions
+// share the reciprocal of r.
+template <int MODE>
+__device__ __forceinline__ void givens_core(double a, double b, double &c, double &s, double &r)
+{
     constexpr bool m1 = MODE == 1;
     const double x = fma(a, a, b * b);
     // square root of x
@@ -87,22 +88,29 @@ __device__ __forceinline__ void givens_fast(double a, double b, double &c, doubl
     g = fma(d, h, g);
     d = fma(-g, g, x);
     g = fma(d, h, g);
-    const double rs = g;
-    // 1/rs, refined twice
-    double rc = __builtin_amdgcn_rcp(rs);
-    double e = fma(-rs, rc, 1.0);
-    rc = fma(rc, e, rc);
-    e = fma(-rs, rc, 1.0);
+    // 1/g
+    double rc = h + h;
+    const double e = fma(-g, rc, 1.0);
     rc = fma(rc, e, rc);
     auto quot = [&](double n) {
         const double q0 = n * rc;
-        const double rem = fma(-rs, q0, n);
+        const double rem = fma(-g, q0, n);
         return fma(rem, rc, q0);
     };
-    const double p = quot(m1 ? b : a), q = quot(m1 ? a : b);
-    c = p;
-    s = m1 ? q : -q;
-    r = rs;
+    c = quot(m1 ? b : a);
+    s = quot(m1 ? a : -b);
+    r = g;
+}
+
+// The generator, through givens_core when every active lane of the
+// wavefront is in range.
+template <int MODE>
+__device__ __forceinline__ void givens_fast(double a, double b, double &c, double &s, double &r)
+{
+    if (__all(givens_in_range(a, b)))
+        givens_core<MODE>(a, b, c, s, r);
+    else
+        givens_m<MODE>(a, b, c, s, r);
 }
 
 __device__ __forceinline__ void givens(double a, double b, int mode, double &c, double &s, double &r)
