@@ -307,7 +307,7 @@ hipError_t run_rotation_stages(HandleDev *const *hs, int count, bool any_spike, 
     if (e == hipSuccess)
         e = timed(ST_GEN, st, [&] { return launch_gen(hs, count, rows, in_lds, gen_threads, gate, st); });
     if (e == hipSuccess)
-        e = timed(ST_APPLY, st, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, gate, st); });
+        e = timed(ST_APPLY, st, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, any_spike, gate, st); });
     return e;
 }
 
@@ -333,10 +333,10 @@ hipError_t run_split_stages(HandleDev *const *hs, int count, bool any_spike, int
     if (e == hipSuccess) e = hipEventRecord(e2, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(sd, e1, 0);
     if (e == hipSuccess)
-        e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, g1, sd); });
+        e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, any_spike, g1, sd); });
     if (e == hipSuccess) e = hipStreamWaitEvent(sd, e2, 0);
     if (e == hipSuccess)
-        e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, g2, sd); });
+        e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, any_spike, g2, sd); });
     if (e == hipSuccess) e = hipEventRecord(e3, sd);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, e3, 0);
     return e;
@@ -381,7 +381,7 @@ hipError_t run_segment_stages(HandleDev *const *hs, int count, bool any_spike, i
         gk.part = 3 + k;
         e = hipStreamWaitEvent(sd, ev[k], 0);
         if (e == hipSuccess)
-            e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, gk, sd); });
+            e = timed(ST_APPLY, sd, [&] { return launch_apply(hs, count, max_panels, k0, nw, rpl, any_spike, gk, sd); });
     }
     if (e == hipSuccess) e = hipEventRecord(done, sd);
     if (e == hipSuccess) e = hipStreamWaitEvent(st, done, 0);

@@ -17,8 +17,10 @@ hipError_t launch_spike(HandleDev *const *hs, int count, Gate gate, hipStream_t 
 // rows: the largest N of the launch's handles.
 hipError_t launch_gen(HandleDev *const *hs, int count, int64_t rows, bool in_lds, int threads, Gate gate,
                       hipStream_t st);
-hipError_t launch_apply(HandleDev *const *hs, int count, int max_panels, int k0, int nw, int rpl, Gate gate,
-                        hipStream_t st);
+hipError_t launch_apply(HandleDev *const *hs, int count, int max_panels, int k0, int nw, int rpl, bool spike,
+                        Gate gate, hipStream_t st);
+hipError_t launch_apply_staged(HandleDev *const *hs, int count, int max_panels, int k0, int nw, int rpl, bool spike,
+                               Gate gate, hipStream_t st);
 // One-time kernel attributes; call before capturing launches in a graph.
 hipError_t prepare_kernels();
 hipError_t launch_fill_identity(double2 *p, int64_t count, hipStream_t st);

@@ -45,23 +45,31 @@ static void add_chain(std::vector<GenChain> &v, int type, int param, int len)
 // the memory wavefront has waited for a load issued after it), and a store
 // after every earlier load and store of it.  Each block takes the earliest
 // start that satisfies these against all earlier blocks of the side.
-static void stage_starts(std::vector<BlockDesc> &blk, int64_t ncols, int K0, int NW)
+//
+// With `pipes` pipelines block b runs on pipeline b mod pipes, beside the
+// blocks before it: its stages only wait for block b - pipes, but its columns
+// for every earlier block's stores, which the one memory wavefront of all
+// pipelines still issues and waits for in order.
+static void stage_starts(std::vector<BlockDesc> &blk, int64_t ncols, int K0, int NW, int pipes,
+                         int32_t BlockDesc::*first)
 {
     const int U = K0 + 3, DL = U / 3, margin = DL + 3;
     const int64_t none = INT64_MIN / 4;
     std::vector<int64_t> st((size_t)ncols, none), ldf((size_t)ncols, none);
-    int64_t s = 0;  // earliest start of the next block (chunks)
-    for (BlockDesc &d : blk) {
-        d.pad = 0;
+    int64_t s[2] = {0, 0};  // earliest start of the next block of each pipeline (chunks)
+    int64_t latest = 0;
+    for (size_t b = 0; b < blk.size(); ++b) {
+        BlockDesc &d = blk[b];
+        int64_t &free = s[b % (size_t)pipes];
         if (d.lmax < 0) {
-            d.start = (int32_t)s;
+            d.*first = (int32_t)std::max(free, latest);
             continue;
         }
         const int dir = d.phase == 1 ? -1 : 1, col0 = d.base - 1, lam_hi = d.lmax + 1;
         const int C = (lam_hi / 3 + K0 - 1 + U) / U;
         auto load_off = [&](int lam) { return lam < 7 ? -1 : std::max(-1, (lam - 7) / 3 - DL); };
         auto store_off = [&](int lam) { return lam / 3 + (NW - 1) * U + K0; };
-        int64_t need = s * U;  // earliest first front
+        int64_t need = std::max(free, latest) * U;  // earliest first front
         for (int lam = 0; lam <= lam_hi; ++lam) {
             const int64_t c = col0 + (int64_t)dir * lam;
             if (c < 0 || c >= ncols) continue;
@@ -69,14 +77,15 @@ static void stage_starts(std::vector<BlockDesc> &blk, int64_t ncols, int K0, int
             need = std::max<int64_t>(need, std::max(ldf[c], st[c]) + 1 - store_off(lam));
         }
         const int64_t start = (need + U - 1) / U;
-        d.start = (int32_t)start;
+        d.*first = (int32_t)start;
+        latest = start;
         for (int lam = 0; lam <= lam_hi; ++lam) {
             const int64_t c = col0 + (int64_t)dir * lam;
             if (c < 0 || c >= ncols) continue;
             ldf[c] = std::max<int64_t>(ldf[c], start * U + load_off(lam));
             st[c] = start * U + store_off(lam);
         }
-        s = start + C;
+        free = start + C;
     }
 }
 
@@ -248,7 +257,7 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
         for (int ph = 1; ph <= 2; ++ph) {
             int nb = ph == 1 ? P->nb1 : P->nb2;
             for (int b = 0; b < nb; ++b) {
-                BlockDesc d;
+                BlockDesc d{};
                 d.phase = ph;
                 d.base = block_base(ph, b, K);
                 if (ph == 1) {
@@ -272,7 +281,8 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
             }
         }
         P->slots[side] = pos;
-        stage_starts(P->blocks[side], side == 0 ? m : n, K0, NW);
+        stage_starts(P->blocks[side], side == 0 ? m : n, K0, NW, 1, &BlockDesc::start);
+        stage_starts(P->blocks[side], side == 0 ? m : n, K0, NW, 2, &BlockDesc::start2);
     }
     // first slot of each chain on each side (same formula the applier reads)
     for (GenChain &g : ch) {
