@@ -1625,7 +1625,7 @@ hipError_t bhu_record(bdu_ctx *h, hipStream_t st)
            *Z2 = Z1 + ldq * n;
     double *vs = Z2 + ldq * n, *vp = vs + ldq, *vx = vp + ldq, *vg = vx + ldq, *vh = vg + ldq, *va = vh + ldq,
            *vt = va + ldq, *vv = vt + ldq, *vq = vv + ldq, *vz = vq + ldq;
-    double *dot = vz + ldq, *dp = dot + 64, *ep = dp + ldp, *part = ep + ldp;
+    double *dp = vz + ldq, *ep = dp + ldp, *part = ep + ldp;
     hipError_t a = hipSuccess;
     auto A = [&](hipError_t x) {
         if (a == hipSuccess) a = x;
@@ -1639,29 +1639,23 @@ hipError_t bhu_record(bdu_ctx *h, hipStream_t st)
     auto column = [&](int64_t k, int64_t i, int64_t j, double *out) {
         A(launch_bhu_gemv_n(Rv, ldp, j, j, Wm + k, ldp, 1.0, nullptr, -1, vs, part, ldq, st));
         A(launch_bhu_gemv_n(Wm, ldp, n, j, vs, 1, -2.0, nullptr, k, vp, part, ldq, st));
-        A(launch_bhu_gemv_t(cc, n, n, 1, vp, 1.0, dot, st));
-        A(launch_bhu_bmul(d, e, m, n, vp, bb, dot, vx, st));
-        A(launch_bhu_gemv_t(Y, ldq, m, i, vx, 1.0, vg, st));
+        A(launch_bhu_bmul_gemv_t(d, e, m, n, vp, bb, cc, false, vx, Y, ldq, i, vg, st));
         A(launch_bhu_gemv_t(S, ldp, i, i, vg, 1.0, vh, st));
         A(launch_bhu_gemv_n(Y, ldq, m, i, vh, 1, -2.0, vx, -1, out, part, ldq, st));
     };
     for (int64_t k = 0; k < kl && a == hipSuccess; ++k) {
         const int64_t j = std::min(k, kr);
         column(k, k, j, va);
-        A(launch_bhu_house(va, k, m, dp + k, Y + k * ldq, st));
-        A(launch_bhu_gemv_t(Y, ldq, m, k, Y + k * ldq, 2.0, vt, st));
+        A(launch_bhu_house_gemv_t(va, k, m, dp + k, Y + k * ldq, Y, ldq, k, 2.0, vt, st));
         A(launch_bhu_gemv_n(S, ldp, k + 1, k, vt, 1, -1.0, nullptr, k, S + k * ldp, part, ldq, st));
         if (k >= kr) continue;
         // row k after k + 1 left and j right reflectors
         A(launch_bhu_gemv_n(S, ldp, k + 1, k + 1, Y + k, ldq, 1.0, nullptr, -1, vv, part, ldq, st));
         A(launch_bhu_gemv_n(Y, ldq, m, k + 1, vv, 1, -2.0, nullptr, k, vq, part, ldq, st));
-        A(launch_bhu_gemv_t(bb, m, m, 1, vq, 1.0, dot, st));
-        A(launch_bhu_btmul(d, e, n, vq, cc, dot, vz, st));
-        A(launch_bhu_gemv_t(Wm, ldp, n, j, vz, 1.0, vg, st));
+        A(launch_bhu_bmul_gemv_t(d, e, m, n, vq, bb, cc, true, vz, Wm, ldp, j, vg, st));
         A(launch_bhu_gemv_t(Rv, ldp, j, j, vg, 1.0, vh, st));
         A(launch_bhu_gemv_n(Wm, ldp, n, j, vh, 1, -2.0, vz, -1, va, part, ldq, st));
-        A(launch_bhu_house(va, k + 1, n, ep + k, Wm + k * ldp, st));
-        A(launch_bhu_gemv_t(Wm, ldp, n, k, Wm + k * ldp, 2.0, vt, st));
+        A(launch_bhu_house_gemv_t(va, k + 1, n, ep + k, Wm + k * ldp, Wm, ldp, k, 2.0, vt, st));
         A(launch_bhu_gemv_n(Rv, ldp, k + 1, k, vt, 1, -1.0, nullptr, k, Rv + k * ldp, part, ldq, st));
     }
     // e_{n-1} (and d_n when m = n) from column n of the final matrix
@@ -1692,7 +1686,7 @@ extern "C" int bdu_update_householder(bdu_handle h, const double *b, const doubl
     HIPCHK(h, wait_dep(h));
     const int64_t m = h->m, n = h->n, ldq = h->hd.ldq, ldp = h->hd.ldp;
     if (!h->bhu) {
-        const int64_t total = n * (3 * ldq + 3 * ldp) + 10 * ldq + 64 + 2 * ldp + (n + 127) / 128 * ldq;
+        const int64_t total = n * (3 * ldq + 3 * ldp) + 10 * ldq + 2 * ldp + (n + 127) / 128 * ldq;
         if (dalloc(h, &h->bhu, total) != hipSuccess) {
             (void)hipGetLastError();
             return BDU_ENOMEM;
@@ -1703,7 +1697,7 @@ extern "C" int bdu_update_householder(bdu_handle h, const double *b, const doubl
     HIPCHK(h, copy_in(h->hd.cst, c, sizeof(double) * n, st));
     const int fin = check_finite(h, {{h->hd.bst, m}, {h->hd.cst, n}}, st);
     if (fin != BDU_OK) return fin;
-    // About 80 000 dependent launches at n = 2048; replaying them from a
+    // About 32 000 dependent launches at n = 2048; replaying them from a
     // recorded graph measured no faster (the chain of dependent kernels on
     // the device, not the host's launch rate, sets the time).
     HIPCHK(h, bhu_record(h, st));
