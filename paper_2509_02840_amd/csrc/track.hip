@@ -58,36 +58,68 @@ __global__ __launch_bounds__(64) void track_combine_kernel(TrackSides s, const d
 
 // xperp_i = x_i - s_i, s_i = sum_j A(i, j) xhat_j (fma, j ascending); one
 // block per chunk of rows, one lane per row (x may be xperp itself: each
-// lane reads its entry before writing it); lane 0 then sums the chunk's
-// x_i^2 and xperp_i^2 in row order (fma from 0) into npart[side][chunk].
-// grid (chunks, 2 sides), kTrackChunk lanes.
+// lane reads its entry before writing it); then the chunk's x_i^2 and
+// xperp_i^2 are summed in row order (fma from 0) into npart[side][chunk], one
+// chain by a lane of each of two wavefronts.  grid (chunks, 2 sides),
+// kTrackChunk lanes.
+//
+// A has to be read once, and 12000 rows are 188 wavefronts: what counts is
+// the loads each has in flight, two groups of 32 columns.  10000 x 2000 and
+// 2000 x 2000: 473 us with a load at a time, 160 us so.
 __global__ __launch_bounds__(kTrackChunk) void track_residual_kernel(TrackSides s, double *npart, int64_t nchunk)
 {
-    __shared__ double sq[kTrackChunk], sx[kTrackChunk];
+    constexpr int G = 32;
+    __shared__ double sq[2][kTrackChunk];  // x, xperp
     const TrackSide &t = s.side[blockIdx.y];
     const int64_t i0 = (int64_t)blockIdx.x * kTrackChunk;
     if (i0 >= t.rows) return;
-    const int64_t i = i0 + threadIdx.x;
-    double xp = 0.0, xv = 0.0;
+    const int64_t i = i0 + threadIdx.x, il = i < t.rows ? i : t.rows - 1;
+    const double *a = t.A + il;
+    double acc = 0.0, u[G], v[G];
+    auto load = [&](double(&x)[G], int64_t j) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) x[q] = a[(j + q < t.cols ? j + q : t.cols - 1) * t.lda];
+    };
+    auto use = [&](const double(&x)[G], int64_t j) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) acc = fma(x[q], t.xhat[j + q], acc);
+    };
+    int64_t j = 0;
+    load(u, 0);
+    for (; j + 2 * G <= t.cols; j += 2 * G) {
+        load(v, j + G);
+        use(u, j);
+        load(u, j + 2 * G);
+        use(v, j + G);
+    }
+    if (j + G <= t.cols) {
+        use(u, j);
+        j += G;
+    }
+    for (; j < t.cols; ++j) acc = fma(a[j * t.lda], t.xhat[j], acc);
+    double xv = 0.0, xp = 0.0;
     if (i < t.rows) {
-        double acc = 0.0;
-        for (int64_t j = 0; j < t.cols; ++j) acc = fma(t.A[i + j * t.lda], t.xhat[j], acc);
         xv = t.x[i];
         xp = xv - acc;
         t.xperp[i] = xp;
     }
-    sq[threadIdx.x] = xp;
-    sx[threadIdx.x] = xv;
+    sq[0][threadIdx.x] = xv;
+    sq[1][threadIdx.x] = xp;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x % 64 == 0 && threadIdx.x < 128) {
+        const double *z = sq[threadIdx.x / 64];
         const int cnt = t.rows - i0 < kTrackChunk ? (int)(t.rows - i0) : kTrackChunk;
-        double p = 0.0, px = 0.0;
-        for (int q = 0; q < cnt; ++q) {
-            px = fma(sx[q], sx[q], px);
-            p = fma(sq[q], sq[q], p);
+        double p = 0.0;
+        int q = 0;
+        for (; q + 16 <= cnt; q += 16) {
+            double w[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) w[k] = z[q + k];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) p = fma(w[k], w[k], p);
         }
-        npart[2 * ((int64_t)blockIdx.y * nchunk + blockIdx.x)] = px;
-        npart[2 * ((int64_t)blockIdx.y * nchunk + blockIdx.x) + 1] = p;
+        for (; q < cnt; ++q) p = fma(z[q], z[q], p);
+        npart[2 * ((int64_t)blockIdx.y * nchunk + blockIdx.x) + threadIdx.x / 64] = p;
     }
 }
 
@@ -237,69 +269,118 @@ __global__ __launch_bounds__(256) void track_truncate_kernel(TrackMiddle mid, in
 // for side 0 and Q for side 1, rm(l) = r - 1 - l, cm(j) = r - 1 - j, and w
 // on side 1 only.
 //
-// Register-tiled outer products: a thread accumulates kProdRows rows (256
-// apart) by kProdCols columns of out, l running in order over the whole
-// sum, so every entry is still the sequential fma chain above.  The block's
-// kProdCols columns of M are staged in LDS kProdChunk rows of l at a time
-// and read as broadcasts; A streams once per block of kProdCols columns.
-// grid (ceil(rows / (256 kProdRows)), ceil(r / kProdCols), 2 sides).
-constexpr int kProdRows = 2, kProdCols = 32, kProdChunk = 64;
+// Register-tiled outer products, l running in order over the whole sum, so
+// every entry is still the sequential fma chain above.  A block of four
+// wavefronts has 64 R rows by 64 columns of out; a lane of wavefront w has R
+// rows (64 apart) by columns 16 w .. 16 w + 15.  kProdChunk terms of A and M
+// at a time are staged in LDS, double buffered, the next ones' loads in
+// flight while these are used; a term's operands are read from there a term
+// ahead (12 reads for 64 fma at R = 4; M is read as broadcasts).
+// 10000 x 2000 and 2000 x 2000 by 2000: 2.81 ms (1.2 ms at the peak of the
+// FP64 units; 3.16 without reading ahead, 3.63 with R = 2, 3.16 with 8 rows
+// by 8 columns a lane), 4.52 ms with two rows and 32 columns a thread and A's
+// loads waited for one by one.  grid (ceil(rows / (64 R)), ceil(r / 64), 2
+// sides).
+constexpr int kProdChunk = 8;
 
-__global__ __launch_bounds__(256) void track_product_kernel(TrackSides s, TrackMiddle mid, const int *kdrop,
-                                                            double *out0, double *out1)
+template <int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void track_product_kernel(
+    TrackSides s, TrackMiddle mid, const int *kdrop, double *out0, double *out1)
 {
-    __shared__ double Ms[kProdChunk][kProdCols];
+    constexpr int ROWS = 64 * R, NA = kProdChunk * ROWS / 256;
+    __shared__ double As[2][kProdChunk][ROWS];
+    __shared__ __attribute__((aligned(16))) double Ms[2][kProdChunk][64];
     const int side = blockIdx.z;
     const TrackSide &t = s.side[side];
-    const int64_t rows = t.rows;
-    const int64_t i0 = (int64_t)blockIdx.x * (256 * kProdRows) + threadIdx.x;
-    if ((int64_t)blockIdx.x * (256 * kProdRows) >= rows) return;  // the other side has more rows
+    const int64_t rows = t.rows, i0 = (int64_t)blockIdx.x * ROWS;
+    if (i0 >= rows) return;  // the other side has more rows
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int r = (int)t.cols;
-    const int j0 = blockIdx.y * kProdCols;
+    const int j0 = blockIdx.y * 64;
     const int k = *kdrop;
     const bool useQ = mid.flip ? side == 1 : side == 0;
     const double *Mb = useQ ? mid.Q : mid.P;
     const int64_t ldm = useQ ? mid.ldq : mid.ldp;
     const bool with_w = mid.flip ? side == 1 : mid.aug[side] != 0;
     auto colof = [&](int j) { return mid.flip ? r - 1 - j : (k >= 0 && j >= k ? j + 1 : j); };
-    double acc[kProdRows][kProdCols];
+    double acc[R][16];
 #pragma unroll
-    for (int q = 0; q < kProdRows; ++q)
+    for (int q = 0; q < R; ++q)
 #pragma unroll
-        for (int c = 0; c < kProdCols; ++c) acc[q][c] = 0.0;
-    for (int l0 = 0; l0 < r; l0 += kProdChunk) {
-        __syncthreads();
-        for (int x = threadIdx.x; x < kProdChunk * kProdCols; x += 256) {
-            const int ll = x % kProdChunk, c = x / kProdChunk, l = l0 + ll, j = j0 + c;
-            Ms[ll][c] = (l < r && j < r) ? Mb[(mid.flip ? r - 1 - l : l) + (int64_t)colof(j) * ldm] : 0.0;
+        for (int c = 0; c < 16; ++c) acc[q][c] = 0.0;
+    // loads past the last row, term or column repeat the last one, for nobody
+    const int arow = tid % ROWS;
+    const double *ap = t.A + (i0 + arow < rows ? i0 + arow : rows - 1);
+    const int ml = tid % kProdChunk, mc = tid / kProdChunk;  // and column mc + 32
+    const double *mp[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int j = j0 + mc + 32 * q;
+        mp[q] = Mb + (int64_t)colof(j < r ? j : r - 1) * ldm;
+    }
+    double av[NA], mv[2];
+    auto load = [&](int l0) {
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            const int l = l0 + tid / ROWS + q * (256 / ROWS);
+            av[q] = ap[(int64_t)(l < r ? l : r - 1) * t.lda];
         }
-        __syncthreads();
-        const int lend = r - l0 < kProdChunk ? r - l0 : kProdChunk;
-        for (int ll = 0; ll < lend; ++ll) {
-            const int64_t col = (int64_t)(l0 + ll) * t.lda;
-            double a[kProdRows];
 #pragma unroll
-            for (int q = 0; q < kProdRows; ++q) {
-                const int64_t i = i0 + 256 * q;
-                a[q] = i < rows ? t.A[i + col] : 0.0;
-            }
-#pragma unroll
-            for (int c = 0; c < kProdCols; ++c) {
-                const double m = Ms[ll][c];
-#pragma unroll
-                for (int q = 0; q < kProdRows; ++q) acc[q][c] = fma(a[q], m, acc[q][c]);
-            }
+        for (int q = 0; q < 2; ++q) {
+            const int l = l0 + ml < r ? l0 + ml : r - 1;
+            mv[q] = mp[q][mid.flip ? r - 1 - l : l];
         }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < NA; ++q) As[buf][tid / ROWS + q * (256 / ROWS)][arow] = av[q];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) Ms[buf][ml][mc + 32 * q] = mv[q];
+    };
+    // a term's operands, read from LDS one term ahead
+    double a[2][R], m[2][16];
+    auto read = [&](int set, int buf, int ll) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) a[set][q] = As[buf][ll][64 * q + lane];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) m[set][c] = Ms[buf][ll][16 * w + c];
+    };
+    auto use = [&](int set) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+#pragma unroll
+            for (int q = 0; q < R; ++q) acc[q][c] = fma(a[set][q], m[set][c], acc[q][c]);
+    };
+    load(0);
+    store(0);
+    __syncthreads();
+    int buf = 0, l0 = 0;
+    for (; l0 + kProdChunk <= r; l0 += kProdChunk) {
+        load(l0 + kProdChunk);
+        read(0, buf, 0);
+#pragma unroll
+        for (int ll = 0; ll < kProdChunk; ++ll) {
+            if (ll + 1 < kProdChunk) read((ll + 1) % 2, buf, ll + 1);
+            __builtin_amdgcn_sched_barrier(0);  // the reads go out before this term's fma
+            use(ll % 2);
+        }
+        store(buf ^ 1);
+        __syncthreads();
+        buf ^= 1;
+    }
+    for (int ll = 0; l0 + ll < r; ++ll) {
+        read(0, buf, ll);
+        use(0);
     }
     double *out = side == 0 ? out0 : out1;
 #pragma unroll
-    for (int c = 0; c < kProdCols; ++c) {
-        const int j = j0 + c;
+    for (int c = 0; c < 16; ++c) {
+        const int j = j0 + 16 * w + c;
         if (j >= r) break;
         const double mw = with_w ? Mb[r + (int64_t)colof(j) * ldm] : 0.0;
 #pragma unroll
-        for (int q = 0; q < kProdRows; ++q) {
-            const int64_t i = i0 + 256 * q;
+        for (int q = 0; q < R; ++q) {
+            const int64_t i = i0 + 64 * q + lane;
             if (i >= rows) continue;
             double v = acc[q][c];
             if (with_w) v = fma(t.xperp[i], mw, v);
@@ -353,9 +434,15 @@ hipError_t launch_track_finish(const TrackSides &s, const TrackMiddle &mid, doub
                                int64_t max_rows, int64_t r, double *out0, double *out1, hipStream_t st)
 {
     hipLaunchKernelGGL(track_truncate_kernel, dim3(1), dim3(256), 0, st, mid, (int)r, d, e, kdrop);
-    hipLaunchKernelGGL(track_product_kernel, dim3((unsigned)((max_rows + 256 * kProdRows - 1) / (256 * kProdRows)),
-                                                   (unsigned)((r + kProdCols - 1) / kProdCols), 2),
-                       dim3(256), 0, st, s, mid, kdrop, out0, out1);
+    // Four rows a lane while that gives every CU a block; else one, for four
+    // times as many blocks (10000 x 2000, r = 64: 19 us, 64 us before)
+    const int64_t cols = (r + 63) / 64;
+    if ((s.side[0].rows + s.side[1].rows) / 256 * cols >= 256)
+        hipLaunchKernelGGL(track_product_kernel<4>, dim3((unsigned)((max_rows + 255) / 256), (unsigned)cols, 2),
+                           dim3(256), 0, st, s, mid, kdrop, out0, out1);
+    else
+        hipLaunchKernelGGL(track_product_kernel<1>, dim3((unsigned)((max_rows + 63) / 64), (unsigned)cols, 2),
+                           dim3(256), 0, st, s, mid, kdrop, out0, out1);
     return hipGetLastError();
 }
 
