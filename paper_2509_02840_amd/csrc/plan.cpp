@@ -48,8 +48,9 @@ static void add_chain(std::vector<GenChain> &v, int type, int param, int len)
 //
 // With `pipes` pipelines block b runs on pipeline b mod pipes, beside the
 // blocks before it: its stages only wait for block b - pipes, but its columns
-// for every earlier block's stores, which the one memory wavefront of all
-// pipelines still issues and waits for in order.
+// for every earlier block's stores (the memory wavefront of each pipeline
+// waits for a load of its own at every front, so the same margin holds
+// between them).
 static void stage_starts(std::vector<BlockDesc> &blk, int64_t ncols, int K0, int NW, int pipes,
                          int32_t BlockDesc::*first)
 {
