@@ -6,7 +6,7 @@
 //                  through LDS so that global reads stay coalesced.
 //  spike_kernel    m > n: the reverse-order rotations that fold u(n+1:m)
 //                  into u(n+1); a dependent chain, one lane.
-//  (gen_kernel, the generation of phases 1 and 2, is in gen.hip.)
+//  (The generation of phases 1 and 2 is in gen.hip.)
 //  apply_kernel    accumulates the rotation streams into Q and P
 //                  (eq. bidiagplus): lanes own rows, a register window of
 //                  columns slides along each block of chains, and the
