@@ -11,6 +11,7 @@
 #include <type_traits>
 
 #include "device.h"
+#include "gen_chains.h"
 #include "kernels.h"
 #include "primitives.h"
 #include "schedule.h"
@@ -101,6 +102,26 @@ __device__ __forceinline__ GenLane gen_lane(const GenChain *chains, int idx)
     l.sr = 16u * (uint32_t)b[2];
     return l;
 }
+
+// A lane among its wavefront's, as gen_chains.h sees it.
+template <typename Place, typename Fetch>
+struct GenWave {
+    GenCursor<GenLane> &lane;
+    Place &at;
+    Fetch &load;
+    template <typename F>
+    __device__ __forceinline__ bool any(F f) const
+    {
+        return __any(f(lane));
+    }
+    template <typename F, typename G>
+    __device__ __forceinline__ void each(F f, G g)
+    {
+        if (f(lane)) g(lane);
+    }
+    __device__ __forceinline__ void place(GenCursor<GenLane> &) { at(); }
+    __device__ __forceinline__ void fetch() { load(); }
+};
 
 // Byte offset of the cell at position s from a step's base pointer, e = s
 // less R times the base's index (which phase 1 lowers by 8 to keep the
@@ -285,27 +306,26 @@ __global__ __launch_bounds__(kGenThreads) void gen_lds_kernel(HandleDev *const *
                 l = gen_lane(h->chains, P1 ? c : nch1 + 1 + c - (c > 2 * n - 3 ? 1 : 0));
             return l;
         };
-        int ci = tid;
-        GenLane cur = chain(ci);
-        while (ci + nt < nch && cur.tau + cur.len <= tb) {
-            ci += nt;
-            cur = chain(ci);
-        }
+        GenCursor<GenLane> my;
+        my.ci = tid;
+        my.nt = nt;
+        my.nch = nch;
+        gen_first_chain(my, tb, chain);
+        const int &ci = my.ci, &q0 = my.q0;
+        const GenLane &cur = my.cur;
         if (cur.tau < tb && cur.tau + cur.len > tb) {  // in flight since an earlier part
             a = h->carry[4 * tid];
             bg = h->carry[4 * tid + 1];
             b = h->carry[4 * tid + 2];
             g = h->carry[4 * tid + 3];
         }
-        bool more = ci + nt < nch;
-        GenLane nxt = chain(ci + nt);
         // wait here for everything loaded: a load in flight in the loop
         // would make it wait for the coefficient stores, which the same
         // counter counts
-        asm volatile("" ::"v"(a), "v"(bg), "v"(b), "v"(g), "v"(nxt.len), "v"(nxt.tau), "v"(nxt.sl), "v"(nxt.sr));
+        asm volatile("" ::"v"(a), "v"(bg), "v"(b), "v"(g), "v"(my.nxt.len), "v"(my.nxt.tau), "v"(my.nxt.sl),
+                     "v"(my.nxt.sr));
 
         LdsPtr p1, p2;
-        int q0 = 0;
         uint32_t oe, oo;  // stream offsets of the even ticks' side and the odd ticks'
         // cell M[s + k] of a lane, e = k plus the tick's constant part of s
         auto cell = [&](LdsPtr p, int e) -> LdsPtr { return p + gen_offset<CAP, P1>(e) / 8; };
@@ -473,9 +493,9 @@ __global__ __launch_bounds__(kGenThreads) void gen_lds_kernel(HandleDev *const *
             one(std::integral_constant<int, 6>{});
             one(std::integral_constant<int, 7>{});
         };
-        // rotation, cells and slots of chain ci at the step from tick t
+        // rotation, cells and slots of the lane's chain at the step from tick t
         auto place = [&](int t) {
-            q0 = t - cur.tau;
+            my.q0 = t - cur.tau;
             // base of the step's cells: its position without the constant part, over R
             const int beta = P1 ? (ci - 3 * q0) >> 2 : (ci + 3 * q0) >> 3;
             p1 = m1 + beta - (P1 ? 8 : 0);
@@ -483,22 +503,16 @@ __global__ __launch_bounds__(kGenThreads) void gen_lds_kernel(HandleDev *const *
             oe = bias + (P1 ? cur.sr : cur.sl) + K16 * (uint32_t)((t >> 1) - ((cur.tau + 1) >> 1));
             oo = bias + (P1 ? cur.sl : cur.sr) + K16 * (uint32_t)((t >> 1) - (cur.tau >> 1));
         };
+        auto fetch_next = [&]() {
+            my.more = ci + nt < nch;
+            my.nxt = chain(ci + nt);
+            asm volatile("" ::"v"(my.nxt.len), "v"(my.nxt.tau), "v"(my.nxt.sl), "v"(my.nxt.sr));
+        };
         place(tb);
         for (int t = tb; t < te; t += kGenStep) {
-            if (__any(more && q0 >= cur.len)) {
-                if (more && q0 >= cur.len) {
-                    ci += nt;
-                    cur = nxt;
-                    more = false;
-                    place(t);
-                }
-                if (!__any(more)) {
-                    // every lane has taken its next chain: fetch the one after
-                    more = ci + nt < nch;
-                    nxt = chain(ci + nt);
-                    asm volatile("" ::"v"(nxt.len), "v"(nxt.tau), "v"(nxt.sl), "v"(nxt.sr));
-                }
-            }
+            auto place_now = [&]() { place(t); };
+            GenWave<decltype(place_now), decltype(fetch_next)> wave{my, place_now, fetch_next};
+            gen_next_chain(wave);
             const bool touched = q0 > -kGenStep && q0 < cur.len;
             const bool starts = touched && q0 <= 0, ends = touched && q0 + kGenStep >= cur.len;
             const uint64_t any = __builtin_amdgcn_ballot_w64(touched);
@@ -511,7 +525,7 @@ __global__ __launch_bounds__(kGenThreads) void gen_lds_kernel(HandleDev *const *
                     else step(std::integral_constant<int, 3>{});
                 }
             }
-            q0 += kGenStep;
+            my.q0 += kGenStep;
             p1 += P1 ? -3 * kGenStep / 4 : 3 * kGenStep / 8;
             p2 += P1 ? -3 * kGenStep / 4 : 3 * kGenStep / 8;
             oe += kGenStep / 2 * K16;
