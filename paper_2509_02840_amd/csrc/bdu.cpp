@@ -50,16 +50,16 @@ struct PlanEntry {
     std::unique_ptr<Plan> plan;
     bool uploaded = false;
 };
-std::map<std::tuple<int64_t, int64_t, int, int>, PlanEntry> g_plans;
+std::map<std::tuple<int64_t, int64_t, int, int, bool>, PlanEntry> g_plans;  // last: generated in LDS if the rows fit
 
 Plan *get_plan(int64_t m, int64_t n, int k0, int nw, bool upload, hipError_t *err)
 {
     std::lock_guard<std::mutex> lk(g_mu);
-    auto key = std::make_tuple(m, n, k0, nw);
+    auto key = std::make_tuple(m, n, k0, nw, g_gen_lds);
     auto it = g_plans.find(key);
     if (it == g_plans.end()) {
         PlanEntry e;
-        e.plan = build_plan(m, n, k0, nw, kGenThreads);
+        e.plan = build_plan(m, n, k0, nw, kGenThreads, g_gen_lds);
         it = g_plans.emplace(key, std::move(e)).first;
     }
     Plan *p = it->second.plan.get();
@@ -465,12 +465,6 @@ void release_streams(bdu_ctx *h)
     h->side = nullptr;
 }
 
-bool gen_lds_fits(int64_t N)
-{
-    std::lock_guard<std::mutex> lk(g_mu);
-    return g_gen_lds && N <= kMaxGenLdsRows;
-}
-
 // Applier tiling for a new handle of shape (m, n).
 void tiling_for(int64_t m, int64_t n, int *k0, int *nw, int *rpl)
 {
@@ -781,7 +775,7 @@ int create_impl(int64_t m, int64_t n, const double *Q, const double *d, const do
     h->n = n;
     h->plan = plan;
     h->rpl = rpl;
-    h->lds_gen = gen_lds_fits(plan->N);
+    h->lds_gen = plan->in_lds;
     HandleDev &hd = h->hd;
     hipError_t a = hipSuccess;
     auto A = [&](hipError_t x) { if (a == hipSuccess) a = x; };

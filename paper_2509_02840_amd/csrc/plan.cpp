@@ -201,7 +201,7 @@ static void chunk_ticks(Plan &P)
 // 8 are best from n = 257 up, 4 below (n = 129: 0.82 ms against 0.85).
 constexpr int kSegments = 8, kSegmentsSmall = 4;
 
-std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_threads)
+std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_threads, bool allow_lds)
 {
     auto P = std::make_unique<Plan>();
     P->m = m;
@@ -212,6 +212,7 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
     P->K = K0 * NW;
     P->S = K0 + 3;
     P->L = gen_threads;
+    P->in_lds = allow_lds && P->N <= kMaxGenLdsRows;
     const int N = (int)P->N, nn = (int)n;
 
     // ---- chains ---------------------------------------------------------
@@ -231,7 +232,10 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
     // the workgroup only needs that many (rounded to whole wavefronts):
     // fewer wavefronts meet at every barrier.
     P->L = (int)std::min<int64_t>(gen_threads, std::max<int64_t>(64, ((int64_t)ch.size() + 63) / 64 * 64));
-    if (P->N <= kMaxGenLdsRows) chunk_ticks(*P);
+    // The device-memory kernel has a barrier at every tick and gains nothing
+    // from the chunked starts, only their extra ticks (n = 2048: 18 749 instead
+    // of 17 727, 35.3 against 34.9 ms an update; n = 400: 3.24 against 3.13).
+    if (P->in_lds) chunk_ticks(*P);
     else scan_ticks(*P);
     const int64_t tend = P->ticks;
     // Phase 1 (with the fold) ends at the tick its last chain finishes; the
@@ -323,7 +327,7 @@ std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_t
         int prev_c = 0;
         for (int k = 1; k <= want; ++k) {
             const int c = k == want ? nbt : (int)((int64_t)nbt * k / want);
-            const int64_t t = k == want ? P->ticks : P->N <= kMaxGenLdsRows ? up(done[c - 1]) : done[c - 1];
+            const int64_t t = k == want ? P->ticks : P->in_lds ? up(done[c - 1]) : done[c - 1];
             if (c <= prev_c || t <= prev_t || (k < want && t >= P->ticks)) continue;
             P->bcut[P->nseg] = c;
             P->tcut[P->nseg] = (int32_t)t;

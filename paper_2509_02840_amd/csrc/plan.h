@@ -14,6 +14,7 @@ struct Plan {
     int64_t m = 0, n = 0, N = 0;
     int K0 = 0, NW = 0, K = 0, S = 0;
     int L = 0;                      // generation threads
+    bool in_lds = false;            // generated by the in-LDS kernel
     std::vector<GenChain> chains;   // non-empty chains in schedule order (with the fold)
     int64_t ticks = 0;              // generation ticks
     int64_t split = 0;              // tick where phase 1 ends with nothing in flight (0: no split)
@@ -31,7 +32,9 @@ struct Plan {
     BlockDesc *d_blocks[2] = {nullptr, nullptr};
 };
 
-// Build (no device work).  gen_threads is the number of generation threads.
-std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_threads);
+// Build (no device work).  gen_threads is the number of generation threads;
+// the ticks are those of the in-LDS kernel if it may be used and the rows fit,
+// else of the device-memory kernel.
+std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_threads, bool allow_lds = true);
 
 }  // namespace bdu
