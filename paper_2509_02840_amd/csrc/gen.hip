@@ -7,7 +7,6 @@
 // large for LDS) with a barrier for every tick.  FP64 throughout.
 #include <hip/hip_runtime.h>
 
-#include <mutex>
 #include <type_traits>
 
 #include "device.h"
@@ -15,6 +14,7 @@
 #include "kernels.h"
 #include "primitives.h"
 #include "schedule.h"
+#include "until_done.h"
 
 namespace bdu {
 
@@ -939,17 +939,17 @@ static_assert(kMaxGenLdsRows == 3392, "the largest capacity");
 
 hipError_t prepare_kernels()
 {
-    static std::once_flag once;
-    static hipError_t status = hipSuccess;
-    std::call_once(once, [] {
-#define BDU_GEN_ATTR(C)                                                                                     \
-    if (status == hipSuccess)                                                                               \
-        status = hipFuncSetAttribute((const void *)gen_lds_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                     GenLds<C>::BYTES);
+    static UntilDone once;
+    return once([] {
+        hipError_t e = hipSuccess;
+#define BDU_GEN_ATTR(C)                                                                                       \
+    if (e == hipSuccess)                                                                                      \
+        e = hipFuncSetAttribute((const void *)gen_lds_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                GenLds<C>::BYTES);
         BDU_GEN_CAPS(BDU_GEN_ATTR)
 #undef BDU_GEN_ATTR
+        return e;
     });
-    return status;
 }
 
 hipError_t launch_gen(HandleDev *const *hs, int count, int64_t rows, bool in_lds, int threads, Gate gate,
