@@ -42,9 +42,9 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # 256 CUs x 128 FP64 flop/clk x 2.4 GHz
 # the counter reads for a plain 1 GiB device copy (bench.py --copy-probe).
 # Valid only for the sources with this digest and the workload named;
 # otherwise the traffic is reported as null.
-TRAFFIC_SOURCES = ["paper_2509_02840_amd/csrc/kernels.hip", "paper_2509_02840_amd/csrc/primitives.h",
-                   "paper_2509_02840_amd/csrc/schedule.h", "paper_2509_02840_amd/csrc/device.h",
-                   "paper_2509_02840_amd/csrc/plan.cpp", "paper_2509_02840_amd/csrc/bdu.cpp"]
+TRAFFIC_SOURCES = ["paper_2509_02840_amd/csrc/" + f
+                   for f in ("apply_kernel.h", "apply.hip", "apply_k84.hip", "apply_k180.hip", "kernels.h", "kernels.hip",
+                             "primitives.h", "schedule.h", "device.h", "plan.h", "plan.cpp", "bdu.cpp")]
 MEASURED_TRAFFIC = {"sha256": "cef9529b2487179606c055ab0defff1f899c18220473f652ba7bd510cd4d777e", "n": 2048, "streams": 64,
                     "bytes": {(12, 15, 1): 27503370709.8, (12, 7, 1): 54759873861.9}}
 
