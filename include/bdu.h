@@ -181,11 +181,12 @@ int bdu_get_tiling(int *k0, int *nw, int *rpl);
  * bdu_handle_tiling reports the tiling a handle was created with. */
 int bdu_autotune(int64_t m, int64_t n, int streams, int64_t *out);
 
-/* Where the rotation generator keeps the working band (offsets -2..3) and
- * u, v, about 64 bytes per row: allow = 1 (default) in LDS when they fit
- * (up to 3392 rows), else in device memory; allow = 0 always in device
- * memory.  Applies to handles created afterwards; results do not depend on
- * it. */
+/* Where the rotation generator keeps the working band and u, v: allow = 1
+ * (default) in LDS when they fit (48 bytes for each of N = n rows when m = n,
+ * n + 1 when m > n, up to N = 3392, whatever m is), else in device memory;
+ * allow = 0 always in device memory.  Applies to handles created afterwards,
+ * and to bdu_plan_stats, _rotations and _segments, which report the ticks of
+ * the generator in use; results do not depend on it. */
 int bdu_set_generation_in_lds(int allow);
 
 /* Split passes: with on >= 1, a handle with n >= 32 whose schedule ends phase 1

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(64) void spike_apply_kernel(HandleDev *const *hs, G
 
 }  // namespace
 
-// Instances in files of their own: each is minutes of compilation.
+// Instances in files of their own, compiled beside each other (half a minute each).
 hipError_t launch_apply_k84(HandleDev *const *hs, int count, int panels, int G, int P, Gate gate, hipStream_t st);
 hipError_t launch_apply_k180(HandleDev *const *hs, int count, int panels, int G, Gate gate, hipStream_t st);
 
@@ -65,7 +65,9 @@ hipError_t launch_apply_staged(HandleDev *const *hs, int count, int max_panels, 
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // Which split: kFill workgroups leave a few CUs to the generator, which
+    // Which split, by the launch's 64-row panels (the largest handle's, times the
+    // handles: a batch of mixed sizes, or a pass that only some of its handles
+    // take, has fewer): kFill workgroups leave a few CUs to the generator, which
     // runs beside this kernel and needs a CU of its own (a launch of 256
     // slowed it from 5.3 to 6.7 ms at n = 2048, and itself with it).
     //   K = 84: G 4 while that leaves at most one workgroup per CU (n = 1024:

@@ -26,7 +26,8 @@
 // pairs by the memory wavefront's loads of every line for three blocks:
 //   n = 2048, K = 180        9.5 -> 6.3 ms (G 3, P 2: 196 workgroups)
 //   4000 x 2000, K = 84     13.9 -> 8.4 ms (G 1, P 2)
-//   10000 x 2000, K = 84    16.9 -> 10.3 ms (G 1, P 2)
+//   10000 x 2000, K = 84    16.9 -> 9.9 ms (G 1, P 2; 1.0 ms of it the spike's
+//                           rotations, in a kernel of their own, apply.hip)
 //   n = 200, K = 84          420 -> 325 us (G 4)
 //   64 streams of n = 2048, K = 180: 153 -> 143 ms (G 1, P 1)
 //

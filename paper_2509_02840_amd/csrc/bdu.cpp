@@ -1691,9 +1691,11 @@ extern "C" int bdu_update_householder(bdu_handle h, const double *b, const doubl
     HIPCHK(h, copy_in(h->hd.cst, c, sizeof(double) * n, st));
     const int fin = check_finite(h, {{h->hd.bst, m}, {h->hd.cst, n}}, st);
     if (fin != BDU_OK) return fin;
-    // About 32 000 dependent launches at n = 2048; replaying them from a
-    // recorded graph measured no faster (the chain of dependent kernels on
-    // the device, not the host's launch rate, sets the time).
+    // About 41 000 dependent launches at n = 2048 (14 a step up to 512
+    // reflectors, 22 beyond, where a product's chunks are added by a second
+    // launch).  Replaying the 80 000 of an earlier form from a recorded graph
+    // measured no faster: the chain of dependent kernels on the device, not the
+    // host's launch rate, sets the time.
     HIPCHK(h, bhu_record(h, st));
     return BDU_OK;
 }
