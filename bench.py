@@ -45,7 +45,7 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6  # 256 CUs x 128 FP64 flop/clk x 2.4 GHz
 TRAFFIC_SOURCES = ["paper_2509_02840_amd/csrc/" + f
                    for f in ("apply_kernel.h", "apply.hip", "apply_k84.hip", "apply_k180.hip", "kernels.h", "kernels.hip",
                              "primitives.h", "schedule.h", "device.h", "plan.h", "plan.cpp", "bdu.cpp")]
-MEASURED_TRAFFIC = {"sha256": "236a9f52266b8de6ae12aff7203952b7ff5f766ef23179b82ec8d6042bed0948", "n": 2048, "streams": 64,
+MEASURED_TRAFFIC = {"sha256": "43ea9deb16b305ba981d673731e95a7cb6fda606cd73f28b00b07b0294dd9194", "n": 2048, "streams": 64,
                     "bytes": {(12, 15, 1): 26625000000, (12, 7, 1): 54584000000}}
 
 

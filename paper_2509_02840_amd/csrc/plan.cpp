@@ -197,8 +197,9 @@ static void chunk_ticks(Plan &P)
 
 // Segments of a single-handle pass (more segments hide more of the
 // application behind generation; each costs a generation launch with its
-// band save and reload and an applier launch).  Measured on one stream:
-// 8 are best from n = 257 up, 4 below (n = 129: 0.82 ms against 0.85).
+// band save and reload and an applier launch).  Measured on one stream, with
+// the generator before the present one: 8 are best from n = 257 up, 4 below
+// (n = 129: 0.82 ms against 0.85).
 constexpr int kSegments = 8, kSegmentsSmall = 4;
 
 std::unique_ptr<Plan> build_plan(int64_t m, int64_t n, int K0, int NW, int gen_threads, bool allow_lds)
