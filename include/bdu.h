@@ -159,9 +159,10 @@ int64_t bdu_footprint_bytes(int64_t m, int64_t n);
  * nw in {1, 2, 4, 8} with k0 in {6, 12} (except k0 = 6, nw = 8, rpl = 2):
  * every wavefront also loads or stores the matrix columns it needs.
  * "Staged": nw in {3, 7, 15} with k0 = 12 (rpl = 1 only for 15) and
- * nw in {3, 5, 7} with k0 = 18 (rpl = 1); the workgroup adds one memory
- * wavefront that streams columns and rotation coefficients through LDS for
- * the compute wavefronts.
+ * nw in {3, 5, 7} with k0 = 18 (rpl = 1); nw counts pipeline stages, and a
+ * memory wavefront streams the columns through LDS for them.  With (12, 7, 1)
+ * and (12, 15, 1) a launch of few panels takes smaller ones, or two pipelines
+ * a workgroup, by itself.
  * Default (12, 7, 1).  Applies to handles created afterwards.  Results do
  * not depend on it. */
 int bdu_set_tiling(int k0, int nw, int rpl);
